@@ -20,7 +20,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0        # MI355X HBM3E
-KERNEL_SOURCES = ["paper_2609_37626_amd/csrc/kernels.hip", "paper_2609_37626_amd/csrc/splash_common.hpp",
+KERNEL_SOURCES = ["paper_2609_37626_amd/csrc/attend.hpp", "paper_2609_37626_amd/csrc/device_types.hpp",
+                  "paper_2609_37626_amd/csrc/kernels.hip", "paper_2609_37626_amd/csrc/splash_common.hpp",
                   "paper_2609_37626_amd/csrc/kernels.hpp"]
 BF16_PEAK_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 METRIC = "us/step and achieved KV GB/s + MFMA TFLOP/s (% of roofline), paged MLA decode"

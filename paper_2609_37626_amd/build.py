@@ -2,23 +2,26 @@
 
 Usage: python -m paper_2609_37626_amd.build
 """
+import concurrent.futures
 import os
 import shutil
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libsplash_attn.so")
-SOURCES = ["api.cpp", "kernels.hip", "dop.hip"]
+SOURCES = ["attend_bf16.hip", "attend_fp8.hip", "attend_latent.hip", "attend_bf16_topk.hip", "attend_fp8_topk.hip",
+           "attend_latent_topk.hip", "attend_exact_qk.hip", "kernels.hip", "api.cpp", "dop.hip"]
 # measurement helpers for the benchmark, a library of their own
 CALIB_LIB = os.path.join(HERE, "libsplash_calib.so")
 CALIB_SOURCES = ["calib.hip"]
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Wall", "-Wno-unused-command-line-argument",
     # keep hipcc from emitting packed fp32 arithmetic
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -40,8 +43,20 @@ def build(verbose: bool = False) -> str:
 
 
 def _compile(sources, lib, verbose: bool) -> str:
+    """Each source to an object of its own, side by side, then one link."""
     tmp = lib + ".tmp"
-    cmd = [hipcc()] + HIPCC_FLAGS + [os.path.join(CSRC, s) for s in sources] + ["-o", tmp]
+    cc = [hipcc()] + HIPCC_FLAGS
+    with tempfile.TemporaryDirectory() as objects:
+        objs = [os.path.join(objects, s + ".o") for s in sources]
+        cmds = [cc + ["-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(sources, objs)]
+        with concurrent.futures.ThreadPoolExecutor(len(cmds)) as pool:
+            list(pool.map(lambda cmd: _run(cmd, verbose), cmds))
+        _run(cc + ["-shared"] + objs + ["-o", tmp], verbose)
+    os.replace(tmp, lib)
+    return lib
+
+
+def _run(cmd, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -51,8 +66,6 @@ def _compile(sources, lib, verbose: bool) -> str:
         raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
     if verbose and msgs:
         print("\n".join(msgs))
-    os.replace(tmp, lib)
-    return lib
 
 
 if __name__ == "__main__":

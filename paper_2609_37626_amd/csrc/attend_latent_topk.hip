@@ -1,0 +1,10 @@
+// attend_kernel over the fp8 latent-row cache, QK on the fp8 pipe, listed positions.
+#include "attend.hpp"
+
+namespace splash {
+
+void launch_attend_latent_topk(const AttendLaunch& a, int32_t workers, hipStream_t s) {
+  launch_attend_heads<true, true, true, true>(a, workers, s);
+}
+
+}  // namespace splash
