@@ -209,14 +209,18 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanLaunch p) {
   // 64 (w >> 3) + j over t = (w & 7) + 8i.  The slices meet in LDS; wave 0
   // adds them up, prices every size (one lane each) and takes the argmin.
   if (wave == 0) {
-    int32_t nd = 0;
+    int32_t nd = 0, before = 0;  // before: the last size of the round before
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
       const int k = 64 * r + lane;
       int32_t ck = 0;
       if (k < kNumCandidates) {
         ck = plan_candidate_size(s_parts[k], max_pages, p.unit_cap);
-        if (k > 0 && plan_candidate_size(s_parts[k - 1], max_pages, p.unit_cap) == ck) ck = 0;
+      }
+      const int32_t up = __shfl_up(ck, 1, 64), prev = lane == 0 ? before : up;
+      before = __shfl(ck, 63, 64);
+      if (k < kNumCandidates) {
+        if (prev == ck) ck = 0;  // (sizes are at least 1, so k = 0 stays)
       } else if (k == kNumCandidates && p.forced_chunk > 0) {
         ck = p.forced_chunk < p.unit_cap ? p.forced_chunk : p.unit_cap;
       }
@@ -225,7 +229,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanLaunch p) {
       const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(keep >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)keep, 0));
       if (ck > 0) {
         s_list[nd + below] = k;
-        s_udiv[nd + below] = udiv_make((uint32_t)ck);  // once per size
+        s_udiv[nd + below] = udiv_make_small((uint32_t)ck);  // once per size (at most unit_cap <= kMaxUnitPages)
       }
       nd += __builtin_popcountll(keep);
     }

@@ -72,3 +72,27 @@ def test_magic_division_and_candidate_parts(tmp_path):
     res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     print(res.stdout)
     assert res.returncode == 0, res.stdout
+
+
+SMALL_PROGRAM = r"""
+#include <stdio.h>
+#include "splash_common.hpp"
+using namespace splash;
+int main() {
+  for (uint32_t d = 1; d <= (uint32_t)kMaxUnitPages; ++d) {
+    const UDiv a = udiv_make(d), b = udiv_make_small(d);
+    if (a.m != b.m || a.s != b.s || a.d != b.d) { printf("d=%u\n", d); return 1; }
+  }
+  printf("ok\n");
+}
+"""
+
+
+def test_divisors_made_in_double_precision_are_the_integer_ones(tmp_path):
+    src, exe = tmp_path / "small.cpp", tmp_path / "small"
+    src.write_text(SMALL_PROGRAM)
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        pytest.skip("no host compiler")
+    subprocess.run([cxx, "-O1", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)], capture_output=True, text=True).stdout == "ok\n"
