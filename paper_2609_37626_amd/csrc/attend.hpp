@@ -120,11 +120,41 @@ __device__ __forceinline__ float head_sum(float v) {
 // products to about 2^-18 of their magnitude sum (measured), where the bf16
 // MFMA keeps fp32: a score is off by up to about 2^-18 * sum |q_i k_i| * scale.
 
-// N pairs of bf16 values (one pair per dword of w, low half first) times
-// `inv` -> hi codes and lo codes (residual times 2^4), value v at byte v % 4
-// of dword v / 4.
+// N pairs of bf16 values (one pair per dword of w, low half first) -> hi
+// codes of the values over `unit` (a power of two) and lo codes (the residual
+// over unit / 16), value v at byte v % 4 of dword v / 4.  The conversions
+// apply the scales themselves and the residual is taken in the values' own
+// units, where it is exact: seven operations a pair (eleven with the scalings
+// on their own), all of it latency at a unit's start.
 template <int N>
-__device__ __forceinline__ void split_query_values(const int* w, int* hi, int* lo, float inv) {
+__device__ __forceinline__ void split_query_values(const int* w, int* hi, int* lo, float unit) {
+  const float unit_lo = unit * 0.0625f;
+#pragma unroll
+  for (int g = 0; g < N / 2; ++g) {
+    const uint32_t d0 = (uint32_t)w[2 * g], d1 = (uint32_t)w[2 * g + 1];
+    s16x2 a = {0, 0};
+    a = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(a, __builtin_bit_cast(bf16x2, d0), unit, false);
+    a = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(a, __builtin_bit_cast(bf16x2, d1), unit, true);
+    const int hw = __builtin_bit_cast(int, a);
+    const f32x2 h01 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hw, unit, false);
+    const f32x2 h23 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hw, unit, true);
+    s16x2 v = {0, 0};
+    v = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(v, __uint_as_float(d0 << 16) - h01[0],
+                                                 __uint_as_float(d0 & 0xFFFF0000u) - h01[1], unit_lo, false);
+    v = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(v, __uint_as_float(d1 << 16) - h23[0],
+                                                 __uint_as_float(d1 & 0xFFFF0000u) - h23[1], unit_lo, true);
+    hi[g] = hw;
+    lo[g] = __builtin_bit_cast(int, v);
+  }
+}
+
+// The same codes from the values scaled by `inv` = 1 / unit first, which the
+// latent-row kernel keeps: with the shorter form the compiler gives its step
+// loop another register assignment, and the whole kernel measures slower (64
+// requests x 2 rows of 2,048 listed positions: 112 against 130 us a pass; the
+// per-token kernel gains from it, chunk 8: 504 -> 488 us).
+template <int N>
+__device__ __forceinline__ void split_query_values_scaled(const int* w, int* hi, int* lo, float inv) {
 #pragma unroll
   for (int g = 0; g < N / 2; ++g) {
     const uint32_t d0 = (uint32_t)w[2 * g], d1 = (uint32_t)w[2 * g + 1];
@@ -248,10 +278,7 @@ struct Ring {
 constexpr int kPBytes = kMaxHeads * kStepKeys * 2;
 
 // Element pairs of the softmax that run under the QK stream (of 8 a step)
-#ifndef SPLASH_P1
-#define SPLASH_P1 2
-#endif
-constexpr int kSoftmaxPairs1 = SPLASH_P1;
+constexpr int kSoftmaxPairs1 = 2;
 
 // Direct global->LDS loads, issued through asm so that the compiler's wait
 // insertion (which cannot tell which LDS bytes they write) does not drain
@@ -640,32 +667,49 @@ void attend_kernel(AttendLaunch a) {
   // Q8: the head's row scale, then the split of every block; sets the lane's
   // softmax constant
   auto split_query = [&]() {
-    auto bmax = [](float m, uint32_t w) {
+    // largest magnitude of both halves, as bf16 bit patterns (they order like
+    // the magnitudes)
+    auto bmax = [](uint32_t m, uint32_t w) -> uint32_t {
+      const uint32_t mag = w & 0x7FFF7FFFu;
+      return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, m), __builtin_bit_cast(u16x2, mag)));
+    };
+    auto bmax_f = [](float m, uint32_t w) {
       return fmaxf(m, fmaxf(fabsf(__uint_as_float(w << 16)), fabsf(__uint_as_float(w & 0xFFFF0000u))));
     };
 #pragma unroll
     for (int i = 0; i < kHB; ++i) {
-      float mx = 0.f;
-#pragma unroll
-      for (int m = 0; m < kQT; ++m)
-#pragma unroll
-        for (int d = 0; d < 8; ++d) mx = bmax(bmax(mx, (uint32_t)qh[m][i][d]), (uint32_t)ql[m][i][d]);
+      int biased;  // exponent field of the row's largest magnitude
       if constexpr (LAT) {
+        float mx = 0.f;
+#pragma unroll
+        for (int m = 0; m < kQT; ++m)
+#pragma unroll
+          for (int d = 0; d < 8; ++d) mx = bmax_f(bmax_f(mx, (uint32_t)qh[m][i][d]), (uint32_t)ql[m][i][d]);
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll
-          for (int d = 0; d < 4; ++d) mx = bmax(mx, __builtin_bit_cast(u32x4, qr[p][i])[d]);
+          for (int d = 0; d < 4; ++d) mx = bmax_f(mx, __builtin_bit_cast(u32x4, qr[p][i])[d]);
+        biased = (int)((__float_as_uint(head_max(mx)) >> 23) & 255u);
       } else {
+        uint32_t mb = 0;
 #pragma unroll
-        for (int d = 0; d < 8; ++d) mx = bmax(mx, (uint32_t)qe[i][d]);
+        for (int m = 0; m < kQT; ++m)
+#pragma unroll
+          for (int d = 0; d < 8; ++d) mb = bmax(bmax(mb, (uint32_t)qh[m][i][d]), (uint32_t)ql[m][i][d]);
+#pragma unroll
+        for (int d = 0; d < 8; ++d) mb = bmax(mb, (uint32_t)qe[i][d]);
+        mb = (mb & 0xFFFFu) > (mb >> 16) ? mb & 0xFFFFu : mb >> 16;
+        mb = max(mb, (uint32_t)__shfl_xor((int)mb, 16, 64));
+        mb = max(mb, (uint32_t)__shfl_xor((int)mb, 32, 64));
+        biased = (int)(mb >> 7);
       }
-      mx = head_max(mx);
-      int e = (int)((__float_as_uint(mx) >> 23) & 255u) - 127;  // floor(log2 max), -127 for 0
+      int e = biased - 127;  // floor(log2 max), -127 for 0
       // (every finite bf16 has e <= 127, so the largest scaled value stays
       // under 256; rows below 2^-100 become zeros, their scores ~0 anyway)
       e = e < -100 ? -100 : (e > 127 ? 127 : e);
       const float inv = __uint_as_float((uint32_t)(127 + 7 - e) << 23);   // 2^(7 - e)
-      c2v[i] = c2 * __uint_as_float((uint32_t)(127 - 7 + e) << 23);       // c2 * 2^(e - 7)
+      const float unit = __uint_as_float((uint32_t)(127 - 7 + e) << 23);  // 2^(e - 7)
+      c2v[i] = c2 * unit;
 #pragma unroll
       for (int m = 0; m < kQT; ++m) {
         int w[16], hi[8], lo[8];
@@ -674,7 +718,8 @@ void attend_kernel(AttendLaunch a) {
           w[d] = qh[m][i][d];
           w[8 + d] = ql[m][i][d];
         }
-        split_query_values<16>(w, hi, lo, inv);
+        if constexpr (LAT) split_query_values_scaled<16>(w, hi, lo, inv);
+        else split_query_values<16>(w, hi, lo, unit);
 #pragma unroll
         for (int d = 0; d < 8; ++d) {
           qh[m][i][d] = hi[d];
@@ -697,7 +742,7 @@ void attend_kernel(AttendLaunch a) {
         int w[8], hi[4], lo[4];
 #pragma unroll
         for (int d = 0; d < 8; ++d) w[d] = qe[i][d];
-        split_query_values<8>(w, hi, lo, inv);
+        split_query_values<8>(w, hi, lo, unit);
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
           qe[i][d] = hi[d];
