@@ -605,14 +605,16 @@ int splash_mla_plan_host(const int32_t* seq_lens_host, int32_t q_chunk, const sp
   const int32_t max_pages = mx > 0 ? mx : 1;
   const int32_t cap_units = std::min<int64_t>(max_units, (int64_t)T + max_partials);
   auto evaluate = [&](int32_t c, int64_t* cost) {
-    int64_t W = 0, S = 0;
+    int64_t W = 0, S = 0, M = 0;
+    const int32_t pair = pair_pages(c, max_pages, kPlanCosts);
     for (int32_t t = 0; t < T; ++t) {
       const int32_t n = P[t] > 0 ? ceil_div(P[t], c) : 0;
       W += n;
       S += n > 1 ? n : 0;
+      M += (P[t] > 0 && P[t] <= pair) ? 1 : 0;
     }
     const bool ok = S <= max_partials && W <= (int64_t)T + max_partials;
-    *cost = ok ? plan_cost(c, W, S, total, max_pages, G, kPlanCosts) : INT64_MAX;
+    *cost = ok ? plan_cost(c, W, S, M, total, max_pages, G, kPlanCosts) : INT64_MAX;
   };
   int32_t best_c = 0;
   int64_t best = INT64_MAX;

@@ -137,6 +137,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanLaunch p) {
   __shared__ int32_t s_ufirst[kPlanLdsTiles + 1];  // first unit of each tile (cached case)
   __shared__ int32_t s_sfirst[kPlanLdsTiles];      // first partial slot of each tile (cached case)
   __shared__ int64_t s_w[16][kNumCandidates + 1], s_s[16][kNumCandidates + 1];  // units, split units per tile slice
+  __shared__ int32_t s_m[16][kNumCandidates + 1];  // tiles of at most pair_pages
   __shared__ int32_t s_lhist[kMaxUnitPages + 1];  // units per length
   __shared__ int32_t s_lbase[kMaxUnitPages + 1];  // next queue slot per length
   __shared__ int32_t s_q[kMaxWorkers];            // fold plan: pages of each rank (0 past the last tile)
@@ -252,13 +253,16 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanLaunch p) {
     const int part = wide ? 0 : lane / np2;
     const int slice = wide ? (wave & 7) : wave;
     int64_t W = 0, S = 0;
+    int32_t M = 0;
     if (j < nd) {
       const int32_t ck = s_cand[s_list[j]];
       const UDiv ud = s_udiv[j];
+      const uint32_t pair = (uint32_t)pair_pages(ck, max_pages, kPlanCosts);
       auto count = [&](int32_t P) {
         const int32_t n = (int32_t)udiv((uint32_t)(P + ck - 1), ud);  // ceil(P / c)
         W += n;
         S += (n > 1 || shard) ? n : 0;
+        M += (uint32_t)(P - 1) < pair ? 1 : 0;  // 1 .. pair pages
       };
       if (cached) {
 #pragma unroll 4
@@ -271,10 +275,12 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanLaunch p) {
     for (int off = np2; off < 64; off <<= 1) {
       W += __shfl_xor(W, off, 64);
       S += __shfl_xor(S, off, 64);
+      M += __shfl_xor(M, off, 64);
     }
     if (j < nd && part == 0) {
       s_w[slice][j] = W;
       s_s[slice][j] = S;
+      s_m[slice][j] = M;
     }
   }
   __syncthreads();
@@ -287,12 +293,14 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanLaunch p) {
       const int k = s_list[j];
       const int32_t ck = s_cand[k];
       int64_t W = 0, S = 0;
+      int32_t M = 0;
       for (int sl = 0; sl < nsl; ++sl) {
         W += s_w[sl][j];
         S += s_s[sl][j];
+        M += s_m[sl][j];
       }
       const bool ok = S <= p.ws.max_partials && W <= p.ws.max_units;
-      const int64_t cost = ok ? plan_cost(ck, W, S, total_pages, max_pages, p.G, kPlanCosts) : INT64_MAX;
+      const int64_t cost = ok ? plan_cost(ck, W, S, M, total_pages, max_pages, p.G, kPlanCosts) : INT64_MAX;
       if (k == kNumCandidates) s_cost[kNumCandidates] = cost;
       const int64_t key = (cost == INT64_MAX || k == kNumCandidates) ? INT64_MAX : ((cost << 7) | k);
       best = key < best ? key : best;

@@ -35,7 +35,8 @@ constexpr int kPlanLdsTiles = 8192;  // planner: tile data cached in LDS, and th
 // most c pages; a tile cut into more than one unit writes partials that
 // the combine step merges.  c is chosen by an argmin of an estimated step
 // time over candidate sizes.  The G persistent workers are dealt the units of
-// a queue, so with W units the busiest worker runs R = ceil(W / G) of them: the
+// a queue, so with W units the busiest worker runs R = ceil(W / G) of them (or
+// one, see plan_cost): the
 // estimate is max(R * c, work / G) plus, per unit on that worker, a fixed
 // cost (query load, pipeline fill), per split unit on it the partial write,
 // and the combine's read of all S partials spread over the workers; all in
@@ -131,18 +132,34 @@ SPLASH_HD int32_t plan_candidate(int32_t k, int32_t max_pages) {
   return plan_candidate_size(plan_candidate_parts(k), max_pages);
 }
 
+// The largest whole tile, in pages, of which a worker can run two in the time
+// of one unit of c pages (0: none).
+SPLASH_HD int32_t pair_pages(int32_t c, int32_t max_pages, PlanCosts k) {
+  const int32_t c_eff = c < max_pages ? c : max_pages;
+  const int32_t h = (16 * c_eff - k.unit_x16) / 32;
+  return h > 0 ? h : 0;
+}
+
 // Estimated step time of unit size c (page equivalents * 16 * G), given the
-// number of units W and split units S it produces.
-SPLASH_HD int64_t plan_cost(int32_t c, int64_t W, int64_t S, int64_t total_pages,
+// number of units W, split units S and tiles M of 1 .. pair_pages(c) pages
+// that it produces.
+SPLASH_HD int64_t plan_cost(int32_t c, int64_t W, int64_t S, int64_t M, int64_t total_pages,
                             int32_t max_pages, int32_t G, PlanCosts k) {
-  const int64_t R = ceil_div_u(W, G);                      // units on the busiest worker
+  // Units on the busiest worker.  The queue, longest first, is dealt in a
+  // snake, so W - G units past the first pass join the W - G shortest of it:
+  // if those 2 (W - G) units are all short enough for a pair to take no longer
+  // than one unit of c pages, the second pass costs nothing.  Without this,
+  // batches that mix long and short histories kept to W <= G and to units
+  // longer than they need (48 requests x 2 latent rows of 64 to 32,768
+  // positions: 52 pages against a mean of 38; now 47).
+  const int64_t R = (W > G && 2 * (W - G) <= M) ? 1 : ceil_div_u(W, G);
   const int64_t RS = ceil_div_u(S, G);                     // split units on it, at most R
   const int64_t c_eff = c < max_pages ? c : max_pages;
   const int64_t mean = total_pages * 16;
   // Busiest worker: at most R units of at most c_eff pages, never below the
-  // mean.  (The queue deals the longest units first; a finer estimate of
-  // that packing favoured splitting batches of short histories, but measured
-  // the saving did not cover the partial writes and the combine.)
+  // mean.  (A finer estimate of the packing favoured splitting batches of
+  // short histories, but measured the saving did not cover the partial writes
+  // and the combine.)
   int64_t busy = R * c_eff * 16 * G;
   if (busy < mean) busy = mean;
   return busy + R * k.unit_x16 * G + (RS < R ? RS : R) * k.split_x16 * G + S * k.combine_x16;
