@@ -124,11 +124,13 @@ __device__ __forceinline__ float head_sum(float v) {
 // codes of the values over `unit` (a power of two) and lo codes (the residual
 // over unit / 16), value v at byte v % 4 of dword v / 4.  The conversions
 // apply the scales themselves and the residual is taken in the values' own
-// units, where it is exact: seven operations a pair (eleven with the scalings
-// on their own), all of it latency at a unit's start.
+// units, halved (a hi code of 256 under the largest unit, 2^120, is 2^128,
+// past fp32; half of it is not), where it is exact: seven operations a pair
+// (eleven with the scalings on their own), all of it latency at a unit's start.
 template <int N>
 __device__ __forceinline__ void split_query_values(const int* w, int* hi, int* lo, float unit) {
-  const float unit_lo = unit * 0.0625f;
+  const float unit_half = unit * 0.5f, unit_lo = unit * 0.03125f;
+  auto residual = [](uint32_t bits, float h) { return __builtin_fmaf(__uint_as_float(bits), 0.5f, -h); };
 #pragma unroll
   for (int g = 0; g < N / 2; ++g) {
     const uint32_t d0 = (uint32_t)w[2 * g], d1 = (uint32_t)w[2 * g + 1];
@@ -136,13 +138,13 @@ __device__ __forceinline__ void split_query_values(const int* w, int* hi, int* l
     a = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(a, __builtin_bit_cast(bf16x2, d0), unit, false);
     a = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(a, __builtin_bit_cast(bf16x2, d1), unit, true);
     const int hw = __builtin_bit_cast(int, a);
-    const f32x2 h01 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hw, unit, false);
-    const f32x2 h23 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hw, unit, true);
+    const f32x2 h01 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hw, unit_half, false);
+    const f32x2 h23 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hw, unit_half, true);
     s16x2 v = {0, 0};
-    v = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(v, __uint_as_float(d0 << 16) - h01[0],
-                                                 __uint_as_float(d0 & 0xFFFF0000u) - h01[1], unit_lo, false);
-    v = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(v, __uint_as_float(d1 << 16) - h23[0],
-                                                 __uint_as_float(d1 & 0xFFFF0000u) - h23[1], unit_lo, true);
+    v = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(v, residual(d0 << 16, h01[0]), residual(d0 & 0xFFFF0000u, h01[1]), unit_lo,
+                                                 false);
+    v = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(v, residual(d1 << 16, h23[0]), residual(d1 & 0xFFFF0000u, h23[1]), unit_lo,
+                                                 true);
     hi[g] = hw;
     lo[g] = __builtin_bit_cast(int, v);
   }

@@ -161,6 +161,35 @@ def test_fp8_query_heads_of_very_different_magnitude():
         assert np.abs(lse_x.cpu().numpy() - ref_lse).max() <= 5e-5
 
 
+@pytest.mark.parametrize("kv_dtype", [W.KV_BF16, W.KV_FP8_E4M3, W.KV_FP8_LATENT])
+@pytest.mark.parametrize("heads", [16, 64, 128])
+def test_query_values_at_the_top_of_bf16(heads, kv_dtype):
+    """Query values up to the largest finite bf16 (255 * 2^120) on dims that are
+    zero in the cache: they add nothing, so with the rest of the query times
+    2^118 and the softmax scale times 2^-118 the result is that of the plain
+    query.  (The fp8 split rounds 248 .. 255 up to a code of 256: 2^128 in
+    the query's own units.)  The row's largest value then scales the rest to
+    a quarter of its plain size, where the split is off by at most 2^-14 for
+    values under 2^-6: 2^-12 of the 576 values under 2^-4, N(0, 1) keys, scale
+    0.072: 5e-5 on a score, a twentieth of the LSE bar."""
+    batch = W.make_custom([3, 65, 700], H=heads, kv_dtype=kv_dtype, seed=heads)
+    dims = [0, 37, 130, 300, 511, 512, 540, 575]
+    values = [248.0, -249.0, 250.0, -251.0, 252.0, 253.0, -254.0, 255.0]
+    kv, q = batch.kv.copy(), batch.q.copy()
+    for d in dims:
+        q[..., d] = 0
+        if kv_dtype == W.KV_FP8_LATENT and d >= 512:
+            kv[..., 528 + 2 * (d - 512):530 + 2 * (d - 512)] = 0
+        else:
+            kv[..., d] = 0
+    plain = dataclasses.replace(batch, q=q, kv=kv)
+    top = scale_bf16_bits(q, 118)
+    for i, (d, v) in enumerate(zip(dims, values)):
+        top[:, i::len(dims), d] = W.f32_to_bf16_bits(np.float32(v * 2.0 ** 120))
+    out, lse = gpu_attend(dataclasses.replace(plain, q=top, softmax_scale=batch.softmax_scale * 2.0 ** -118))
+    assert_parity(plain, out, lse, label=f"top of bf16, H {heads}, kv {kv_dtype}")
+
+
 def test_forced_splits_fp8_chunk():
     batch = W.make_custom([700, 2000], H=128, q_chunk=8, kv_dtype=W.KV_FP8_E4M3, seed=22)
     out, lse = gpu_attend(batch, flags=B.FLAG_FORCE_SPLIT, split_pages=4)

@@ -7,10 +7,13 @@ lo = rne(16 (x - hi)), applied as hi + lo / 16 (the lo MFMA carries block
 scale 2^-4).  These tests pin that arithmetic against a plain E4M3 table
 (OCP E4M3: bias 7, 3 mantissa bits, largest finite 448, no infinities), over
 every bf16 value of the range: the split is exact for |x| >= 2^-6 and off by
-at most 2^-14 below, and neither code overflows.  The kernel's use of it is
-checked end to end by the fp8 parity tests on the GPU.
+at most 2^-14 below, and neither code overflows.  The per-token kernel takes
+the residual in the query's own units, halved, in fp32: that form is pinned too,
+for rows from the smallest scaled exponent to the largest finite bf16.  The
+kernels' use of it is checked end to end by the fp8 parity tests on the GPU.
 """
 import numpy as np
+import pytest
 
 
 def e4m3_table():
@@ -77,3 +80,20 @@ def test_row_scale_puts_the_largest_value_in_128_256():
         hi, lo = split(x)
         err = np.abs((hi + lo / 16.0) * 2.0 ** (e - 7) - q)
         assert err.max() <= 2.0 ** -14 * 2.0 ** (e - 7)
+
+
+@pytest.mark.parametrize("e", [-100, -99, -13, 0, 1, 64, 125, 126, 127])
+def test_residual_in_halved_query_units_is_the_scaled_one(e):
+    """What the per-token kernel computes, in fp32: hi over unit = 2^(e - 7),
+    then q / 2 - hi unit / 2 over unit / 32.  Every bf16 value of a row whose
+    largest magnitude has exponent e (all finite ones at e = 127)."""
+    q = all_bf16_below(2.0 ** (e + 1) if e < 127 else np.inf)
+    q32 = q.astype(np.float32)
+    half, lo_unit = np.float32(2.0 ** (e - 8)), np.float32(2.0 ** (e - 12))
+    assert half > np.finfo(np.float32).tiny and lo_unit > np.finfo(np.float32).tiny
+    hi, lo = split(q * 2.0 ** (7 - e))
+    h = hi.astype(np.float32) * half
+    with np.errstate(over="raise"):
+        r = q32 * np.float32(0.5) - h   # (the kernel's fma rounds once: no more than this)
+    assert np.all(np.isfinite(h)) and np.all(np.isfinite(r))
+    assert np.array_equal(rne_e4m3(r.astype(np.float64) / np.float64(lo_unit)), lo)
