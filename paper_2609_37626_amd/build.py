@@ -15,7 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libsplash_attn.so")
 SOURCES = ["attend_bf16.hip", "attend_fp8.hip", "attend_latent.hip", "attend_bf16_topk.hip", "attend_fp8_topk.hip",
-           "attend_latent_topk.hip", "attend_exact_qk.hip", "kernels.hip", "api.cpp", "dop.hip"]
+           "attend_latent_topk.hip", "attend_exact_fp8.hip", "attend_exact_fp8_topk.hip", "attend_exact_latent.hip",
+           "attend_exact_latent_topk.hip", "kernels.hip", "api.cpp", "dop.hip"]
 # measurement helpers for the benchmark, a library of their own
 CALIB_LIB = os.path.join(HERE, "libsplash_calib.so")
 CALIB_SOURCES = ["calib.hip"]

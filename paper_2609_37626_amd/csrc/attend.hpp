@@ -488,6 +488,9 @@ void attend_kernel(AttendLaunch a) {
   constexpr int kHB = NB == 8 ? 2 : 1;   // head blocks a wave owns for QK
   constexpr int kKS = 18;                // 32-dim steps of the bf16 QK
   constexpr int kQT = 4;                 // 128-dim blocks on the fp8 pipe (then the RoPE 64)
+  constexpr bool kExact = FP8 && !Q8;    // exact QK of the fp8 caches: K converted to bf16
+  // (exact QK) K fragment f of a step is one that is converted
+  constexpr auto converts = [](int f) { return f < 36 && !(LAT && f % kKS >= 16); };
   // Unit overlap (dense bf16 and per-token fp8): the next unit's query and
   // first kDist steps are issued before this unit's epilogue stores, so their
   // latency hides behind the epilogue.  (Latent rows: with it the step loop
@@ -1118,7 +1121,6 @@ void attend_kernel(AttendLaunch a) {
           };
           // bf16 K fragment f = 18 kb + ks
           auto load_kf = [&](int f) { return load_k_raw<FP8>(buf, kbase_i, f % kKS, f / kKS); };
-          bf16x8 ka_prev;     // fp8: the converted fragment the previous QK MFMA was issued with
           bf16x8 kr[LAT ? 4 : 1];
           // LAT: tile scales of the lane's key row in each key block (Q8: their
           // biased exponents are the E8M0 bytes)
@@ -1128,6 +1130,19 @@ void attend_kernel(AttendLaunch a) {
             load_tsc(0);
             if constexpr (!Q8) load_tsc(1);
           }
+          // exact QK of the fp8 caches: fragment f converted to bf16 (kc[f % 3];
+          // latent RoPE fragments are bf16 as read), half of it a slot
+          u32x4 kc[kExact ? 3 : 1];
+          auto convert_half = [&](auto fc, auto hc) {
+            constexpr int f = decltype(fc)::value, h = decltype(hc)::value;
+            if constexpr (converts(f)) {
+              const float scale = LAT ? tsc[f / kKS][(f % kKS) >> 2] : 1.0f;
+              const int raw = (int)kf[f % kKPre][h];
+              kc[f % 3][2 * h] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw, scale, false));
+              kc[f % 3][2 * h + 1] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw, scale, true));
+              asm volatile("" : "+v"(kc[f % 3]));
+            }
+          };
           if constexpr (Q8) {
             if constexpr (LAT) {
 #pragma unroll
@@ -1150,6 +1165,13 @@ void attend_kernel(AttendLaunch a) {
               }
             // an fp8 MFMA reads the accumulator a bf16 MFMA wrote: its wait states
             asm volatile("s_nop 7");
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if constexpr (kExact) {
+            convert_half(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+            convert_half(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+            convert_half(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{});
+            kf[0] = load_kf(kKPre);
             __builtin_amdgcn_sched_barrier(0);
           }
           static_for<kSlots1>([&](auto ic) {
@@ -1178,32 +1200,40 @@ void attend_kernel(AttendLaunch a) {
                   if constexpr (LAT && f + 1 == kF) load_tsc(1);
                 }
               }
-            } else {
+            } else if constexpr (kExact) {
+              // Bound by issue: a fragment's four conversions take about as
+              // long as its two MFMAs (8 cycles each against 16), so they are
+              // dealt out between the MFMAs of the two fragments before it and
+              // neither pipe waits for the other.  Two or more instructions
+              // (that slot's second MFMA, the next fragment's conversions)
+              // separate the last one from the first MFMA that reads it; where
+              // none follow, that MFMA brings its wait states.  Against all
+              // four just before the fragment's MFMAs (and their wait states),
+              // 128 heads: 64 requests of 1,024 to 4,096 positions 87.5 -> 79.8
+              // us per-token, 94.8 -> 89.3 latent rows; 8 x 4 rows of 8,192 to
+              // 32,768 positions 224 -> 196 and 252 -> 229 us.
               constexpr int kb = i / kKS, ks = i % kKS;
               bf16x8 ka;
-              if constexpr (LAT) {
-                if constexpr (ks < 16) ka = fp8x8_to_bf16(kf[i % kKPre], tsc[kb][ks >> 2]);
-                else ka = kr[2 * kb + (ks & 1)];
-              } else {
-                ka = frag_bf16<FP8>(kf[i % kKPre]);
+              if constexpr (converts(i)) ka = __builtin_bit_cast(bf16x8, kc[i % 3]);
+              else ka = kr[2 * kb + (ks & 1)];
+              mfma_qk<ks == 0, converts(i) && !converts(i + 1)>(sacc[kb][0], ka, qf[ks][0]);
+              __builtin_amdgcn_sched_barrier(0);
+              convert_half(std::integral_constant<int, i + 1>{}, std::integral_constant<int, 1>{});
+              __builtin_amdgcn_sched_barrier(0);
+              if constexpr (kHB == 2) mfma_qk<ks == 0, false>(sacc[kb][1], ka, qf[ks][1]);
+              __builtin_amdgcn_sched_barrier(0);
+              convert_half(std::integral_constant<int, i + 2>{}, std::integral_constant<int, 0>{});
+              if constexpr (i + 1 + kKPre < 36) {
+                constexpr int n = i + 1 + kKPre;
+                if constexpr (!converts(n)) kr[2 * (n / kKS) + (n & 1)] = load_kr(n / kKS, n & 1);
+                else kf[n % kKPre] = load_kf(n);
               }
-              if constexpr (FP8) {
-                // the conversion must not reuse the registers of the MFMA just
-                // issued (the asm hides that read from the compiler): keeping
-                // that fragment live through it gives this one its own
-                if constexpr (i > 0) asm volatile("" ::"v"(ka), "v"(ka_prev));
-                ka_prev = ka;
-              }
-              if constexpr (i + kKPre < 36) {
-                constexpr int n = i + kKPre;
-                if constexpr (LAT && n % kKS >= 16) kr[2 * (n / kKS) + (n & 1)] = load_kr(n / kKS, n & 1);
-                else kf[i % kKPre] = load_kf(n);
-              }
+            } else {
+              constexpr int kb = i / kKS, ks = i % kKS;
+              const bf16x8 ka = kf[i % kKPre];
+              if constexpr (i + kKPre < 36) kf[i % kKPre] = load_kf(i + kKPre);
 #pragma unroll
-              for (int x = 0; x < kHB; ++x) {
-                if constexpr (ks == 0) mfma_qk<true, FP8>(sacc[kb][x], ka, qf[ks][x]);
-                else mfma_qk<false, FP8>(sacc[kb][x], ka, qf[ks][x]);
-              }
+              for (int x = 0; x < kHB; ++x) mfma_qk<ks == 0, false>(sacc[kb][x], ka, qf[ks][x]);
             }
             stream1_rest(ic);
             __builtin_amdgcn_sched_barrier(0);
@@ -1454,8 +1484,8 @@ void attend_kernel(AttendLaunch a) {
 // The kernel for a call's head count.  Up to 64 (32) heads only 4 (2) head
 // blocks are multiplied, on waves that own one each, instead of 8 with
 // padding (measured: 64 heads over bf16, three layers, 115 -> 99 us; 16 heads
-// over fp8, 219 -> 176 us); the exact QK of the fp8 caches, kept for its sums and
-// not for speed, has the 8-block kernel alone.
+// over fp8, 219 -> 176 us; exact QK, 64 heads over fp8, 82.6 -> 65.4 us, 16
+// heads over latent rows, 305 -> 200 us).
 // NT (non-temporal cache-row loads) when every request has one query row:
 // then no two tiles read the same pages.
 template <bool FP8, bool TOPK, bool LAT, bool Q8>
@@ -1467,13 +1497,9 @@ inline void launch_attend_heads(const AttendLaunch& a, int32_t workers, hipStrea
     else
       hipLaunchKernelGGL((attend_kernel<FP8, TOPK, LAT, false, Q8, NB>), dim3(workers), dim3(256), 0, s, a);
   };
-  if constexpr (FP8 && !Q8) {
-    go(std::integral_constant<int, 8>{});
-  } else {
-    if (a.H > 64) go(std::integral_constant<int, 8>{});
-    else if (a.H > 32) go(std::integral_constant<int, 4>{});
-    else go(std::integral_constant<int, 2>{});
-  }
+  if (a.H > 64) go(std::integral_constant<int, 8>{});
+  else if (a.H > 32) go(std::integral_constant<int, 4>{});
+  else go(std::integral_constant<int, 2>{});
 }
 
 }  // namespace splash

@@ -998,7 +998,8 @@ hipError_t launch_plan(const PlanLaunch& p, hipStream_t s) {
 hipError_t launch_attend(const AttendLaunch& a, int32_t workers, hipStream_t s) {
   // fp8 caches: QK on the fp8 pipe unless the caller asked for the exact one
   const bool topk = a.topk_idx != nullptr;
-  if (a.kv_dtype != 0 && a.exact_qk) launch_attend_exact_qk(a, workers, s);
+  if (a.kv_dtype == 2 && a.exact_qk) (topk ? launch_attend_exact_latent_topk : launch_attend_exact_latent)(a, workers, s);
+  else if (a.kv_dtype == 1 && a.exact_qk) (topk ? launch_attend_exact_fp8_topk : launch_attend_exact_fp8)(a, workers, s);
   else if (a.kv_dtype == 2) (topk ? launch_attend_latent_topk : launch_attend_latent)(a, workers, s);
   else if (a.kv_dtype == 1) (topk ? launch_attend_fp8_topk : launch_attend_fp8)(a, workers, s);
   else (topk ? launch_attend_bf16_topk : launch_attend_bf16)(a, workers, s);

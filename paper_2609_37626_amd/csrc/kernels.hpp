@@ -95,7 +95,10 @@ void launch_attend_fp8(const AttendLaunch& p, int32_t workers, hipStream_t s);
 void launch_attend_fp8_topk(const AttendLaunch& p, int32_t workers, hipStream_t s);
 void launch_attend_latent(const AttendLaunch& p, int32_t workers, hipStream_t s);
 void launch_attend_latent_topk(const AttendLaunch& p, int32_t workers, hipStream_t s);
-void launch_attend_exact_qk(const AttendLaunch& p, int32_t workers, hipStream_t s);
+void launch_attend_exact_fp8(const AttendLaunch& p, int32_t workers, hipStream_t s);
+void launch_attend_exact_fp8_topk(const AttendLaunch& p, int32_t workers, hipStream_t s);
+void launch_attend_exact_latent(const AttendLaunch& p, int32_t workers, hipStream_t s);
+void launch_attend_exact_latent_topk(const AttendLaunch& p, int32_t workers, hipStream_t s);
 hipError_t launch_combine(const CombineLaunch& p, hipStream_t s);
 hipError_t launch_gather(const void* kv, const int32_t* bt, const int32_t* seq_lens, int32_t B,
                          int32_t bt_stride, int32_t row_bytes, void* dense, hipStream_t s);
