@@ -200,6 +200,7 @@ int do_plan(const int32_t* seq_lens, int32_t q_chunk, const splash_mla_desc* d, 
   p.key_end = sh.key_end;
   p.topk_count = sh.topk_count;
   p.unit_cap = sh.topk_idx ? kTopkUnitPages : kMaxUnitPages;
+  p.pair_spread = pair_spread(d->batch, q_chunk, sh.topk_idx != nullptr, sh.key_end != nullptr);
   p.B = d->batch;
   p.q_chunk = q_chunk;
   p.G = G;
@@ -606,7 +607,7 @@ int splash_mla_plan_host(const int32_t* seq_lens_host, int32_t q_chunk, const sp
   const int32_t cap_units = std::min<int64_t>(max_units, (int64_t)T + max_partials);
   auto evaluate = [&](int32_t c, int64_t* cost) {
     int64_t W = 0, S = 0, M = 0;
-    const int32_t pair = pair_pages(c, max_pages, kPlanCosts);
+    const int32_t pair = pair_pages(c, max_pages, pair_spread(B, q_chunk, false, false), false, kPlanCosts);
     for (int32_t t = 0; t < T; ++t) {
       const int32_t n = P[t] > 0 ? ceil_div(P[t], c) : 0;
       W += n;

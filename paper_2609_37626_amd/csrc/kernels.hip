@@ -257,7 +257,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanLaunch p) {
     if (j < nd) {
       const int32_t ck = s_cand[s_list[j]];
       const UDiv ud = s_udiv[j];
-      const uint32_t pair = (uint32_t)pair_pages(ck, max_pages, kPlanCosts);
+      const uint32_t pair = (uint32_t)pair_pages(ck, max_pages, p.pair_spread, shard, kPlanCosts);
       auto count = [&](int32_t P) {
         const int32_t n = (int32_t)udiv((uint32_t)(P + ck - 1), ud);  // ceil(P / c)
         W += n;

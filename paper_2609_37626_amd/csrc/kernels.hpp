@@ -45,6 +45,7 @@ struct PlanLaunch {
   const int32_t* topk_count;  // top-k variant: row n attends its first topk_count[n] selected tokens
   int32_t B, q_chunk, G, forced_chunk;
   int32_t unit_cap;           // largest unit in pages (kMaxUnitPages, or kTopkUnitPages for top-k)
+  int32_t pair_spread;        // see pair_spread()
   Workspace ws;
 };
 

@@ -132,11 +132,26 @@ SPLASH_HD int32_t plan_candidate(int32_t k, int32_t max_pages) {
   return plan_candidate_size(plan_candidate_parts(k), max_pages);
 }
 
-// The largest whole tile, in pages, of which a worker can run two in the time
-// of one unit of c pages (0: none).
-SPLASH_HD int32_t pair_pages(int32_t c, int32_t max_pages, PlanCosts k) {
+// Pages by which a tile of the queue's short end may exceed the shortest row
+// of its request (kMaxUnitPages: the short end is not known to be short).  The
+// queue is ordered longest unit first; with query chunks (at most kMaxWorkers
+// requests, not a shard's) whole requests are, by their longest unit, so that
+// a tile stands where the longest row of its request puts it: a row of a
+// causal chunk is at most q_chunk - 1 keys shorter, a listed one any number.
+// Past kPlanLdsTiles tiles the queue is in tile order.
+SPLASH_HD int32_t pair_spread(int32_t B, int32_t q_chunk, bool listed, bool shard) {
+  if ((int64_t)B * q_chunk > kPlanLdsTiles) return kMaxUnitPages;
+  if (q_chunk == 1 || shard || B > kMaxWorkers) return 0;
+  return listed ? kMaxUnitPages : ceil_div(q_chunk - 1, kPage);
+}
+
+// The longest whole tile, in pages, that counts as one of which a worker can
+// run two in the time of one unit of c pages, its request's rows up to
+// `spread` pages longer (0: none).  partials: whole tiles too write a partial
+// (a shard's).
+SPLASH_HD int32_t pair_pages(int32_t c, int32_t max_pages, int32_t spread, bool partials, PlanCosts k) {
   const int32_t c_eff = c < max_pages ? c : max_pages;
-  const int32_t h = (16 * c_eff - k.unit_x16) / 32;
+  const int32_t h = (16 * c_eff - k.unit_x16 - (partials ? k.split_x16 : 0)) / 32 - spread;
   return h > 0 ? h : 0;
 }
 
@@ -145,10 +160,11 @@ SPLASH_HD int32_t pair_pages(int32_t c, int32_t max_pages, PlanCosts k) {
 // that it produces.
 SPLASH_HD int64_t plan_cost(int32_t c, int64_t W, int64_t S, int64_t M, int64_t total_pages,
                             int32_t max_pages, int32_t G, PlanCosts k) {
-  // Units on the busiest worker.  The queue, longest first, is dealt in a
-  // snake, so W - G units past the first pass join the W - G shortest of it:
-  // if those 2 (W - G) units are all short enough for a pair to take no longer
-  // than one unit of c pages, the second pass costs nothing.  Without this,
+  // Units on the busiest worker.  The queue is dealt in a snake, so its W - G
+  // units past the first pass join the W - G before them.  M whole tiles (no
+  // split unit is under c / 2 pages) stand at the queue's short end, each short
+  // enough for a pair to take no longer than one unit of c pages: if the
+  // 2 (W - G) are among them, the second pass costs nothing.  Without this,
   // batches that mix long and short histories kept to W <= G and to units
   // longer than they need (48 requests x 2 latent rows of 64 to 32,768
   // positions: 52 pages against a mean of 38, 219 us a pass; now 47, 204 us).
