@@ -290,7 +290,10 @@ constexpr int kSoftmaxPairs1 = 2;
 // (4 * lane for the dword form).  SRC_ADD goes into the instruction's offset,
 // which moves the LDS destination as well: M0 is set that much lower.  Three
 // instructions a load: a lone wave on its SIMD pays an issue slot for each.
-// (M0 is the compiler's reserve: it holds nothing there that these kernels use.)
+// (M0 is a reserved register: the compiler allocates nothing to it, writes it
+// only for an instruction that takes it, and refuses it as a clobber.  It is
+// not restored: nothing else in these kernels takes it, which their listing
+// shows as no mention of m0 but these.)
 // NT: the non-temporal hint ("nt" on gfx950), which streams the lines through
 // the caches instead of keeping them; the attend kernel sets it when no other
 // tile reads the same pages (one query row per request), so that the cache
