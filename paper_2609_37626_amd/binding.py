@@ -137,12 +137,15 @@ def _stream(stream) -> Optional[int]:
 
 def _current_stream() -> int:
     """The current HIP stream of the current device, as the C side takes it.
-    (Once the device is initialised, straight from the runtime binding:
-    building a torch Stream object for its handle was a third of the 7.4 us
-    that a regroup call spent on the host.)"""
+    (Once the device is initialised, straight from the runtime binding, where
+    this torch has it: building a torch Stream object for its handle was a
+    third of the 7.4 us that a regroup call spent on the host.)"""
     import torch
     if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
     return torch.cuda.current_stream().cuda_stream
 
 

@@ -402,3 +402,24 @@ def test_noalloc_refusals_happen_on_the_host():
     assert call(B.make_desc(4, 16, 8, 24, flags=B.FLAG_DEBUG_CHECK)) == B.SPLASH_ERR_UNSUPPORTED
     assert call(B.make_desc(0, 16, 8, 24)) == B.SPLASH_OK
     assert B.NOALLOC_SCRATCH_BYTES == 128 << 20
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """The stream's handle comes from the runtime binding once the device is
+    initialised, and from the Stream object before or where torch lacks that."""
+    import torch
+
+    class Stream:
+        cuda_stream = 77
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    assert B._stream(None) == 77
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
+    assert B._stream(None) == 103
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name)
+        assert B._stream(None) == 77
+    assert B._stream(5) == 5 and B._stream(Stream) == 77
