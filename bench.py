@@ -20,9 +20,6 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0        # MI355X HBM3E
-KERNEL_SOURCES = ["paper_2609_37626_amd/csrc/attend.hpp", "paper_2609_37626_amd/csrc/device_types.hpp",
-                  "paper_2609_37626_amd/csrc/kernels.hip", "paper_2609_37626_amd/csrc/splash_common.hpp",
-                  "paper_2609_37626_amd/csrc/kernels.hpp"]
 BF16_PEAK_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 METRIC = "us/step and achieved KV GB/s + MFMA TFLOP/s (% of roofline), paged MLA decode"
 
@@ -31,11 +28,18 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
+def kernel_sources():
+    """What the library is built from: its sources and their headers."""
+    from paper_2609_37626_amd import build
+    return build.SOURCES + sorted(f for f in os.listdir(build.CSRC) if f.endswith(".hpp"))
+
+
 def kernel_source_digest():
     import hashlib
+    from paper_2609_37626_amd import build
     h = hashlib.sha256()
-    for rel in KERNEL_SOURCES:
-        with open(os.path.join(ROOT, rel), "rb") as f:
+    for name in kernel_sources():
+        with open(os.path.join(build.CSRC, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
 

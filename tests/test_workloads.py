@@ -116,3 +116,23 @@ def test_latent_rows_recipe():
     ref = W.make_custom([70, 130, 64], H=16, q_chunk=2, kv_dtype=W.KV_BF16, seed=9)
     assert np.array_equal(b.q, ref.q) and np.array_equal(b.block_table, ref.block_table)
     assert np.array_equal(rows[:, 528:].copy().view('<u2'), ref.kv.reshape(-1, 576)[:, 512:])
+
+
+def test_traffic_digest_covers_every_source_of_the_library(monkeypatch, tmp_path):
+    """The stored counters are taken as current only for the sources they were
+    measured on: a change of any file that the library is built from shows."""
+    import shutil
+
+    import bench
+    from paper_2609_37626_amd import build
+    copy = tmp_path / "csrc"
+    shutil.copytree(build.CSRC, copy)
+    monkeypatch.setattr(build, "CSRC", str(copy))
+    seen = {bench.kernel_source_digest()}
+    for f in sorted(copy.iterdir()):
+        if f.name in build.CALIB_SOURCES:
+            continue
+        f.write_text(f.read_text() + "// changed\n")
+        digest = bench.kernel_source_digest()
+        assert digest not in seen, f.name
+        seen.add(digest)
