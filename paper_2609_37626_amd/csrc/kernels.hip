@@ -37,20 +37,6 @@ extern "C" __device__ __attribute__((const)) long long __ockl_wfred_min_i64(long
 extern "C" __device__ __attribute__((const)) float __ockl_wfred_max_f32(float);
 extern "C" __device__ __attribute__((const)) float __ockl_wfred_add_f32(float);
 
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-template <typename T>
-__device__ __forceinline__ T wave_max(T v) {
-  for (int o = 32; o > 0; o >>= 1) {
-    T w = __shfl_xor(v, o, 64);
-    v = w > v ? w : v;
-  }
-  return v;
-}
-
 // Inclusive scan of one int per lane over the wave with DPP moves: prefix
 // sums inside each row of 16 lanes (shifts 1, 2, 4, 8), then the row totals
 // are broadcast into the following rows.
@@ -230,7 +216,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanLaunch p) {
       const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(keep >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)keep, 0));
       if (ck > 0) {
         s_list[nd + below] = k;
-        s_udiv[nd + below] = udiv_make_small((uint32_t)ck);  // once per size (at most unit_cap <= kMaxUnitPages)
+        s_udiv[nd + below] = udiv_make((uint32_t)ck);  // once per size (at most unit_cap <= kMaxUnitPages)
       }
       nd += __builtin_popcountll(keep);
     }

@@ -66,27 +66,15 @@ SPLASH_HD int32_t ceil_div(int32_t a, int32_t b) { return (a + b - 1) / b; }
 struct UDiv {
   uint32_t m, s, d;
 };
+// The divisors made here are at most kMaxUnitPages, with a double-precision
+// division in place of the 64-bit integer one, which on the device is a long
+// routine (the plan kernel's first wave makes every divisor of a plan before
+// anything else can go on): the dividend stays below 2^42, so the quotient's
+// fraction, at least 1 / 1024 away from an integer it does not equal, survives
+// the rounding to 53 bits and the truncation is exact.  With the candidate
+// sizes divided once each the plan kernel takes 7.8 -> 6.9 us for 4 long
+// histories, 13.2 -> 11.9 for 128 listed rows.
 SPLASH_HD UDiv udiv_make(uint32_t d) {
-  UDiv r;
-  r.d = d;
-  r.m = 0;
-  r.s = 0;
-  if (d >= 2) {
-    const uint32_t l = 32u - (uint32_t)__builtin_clz(d - 1u);  // ceil(log2 d)
-    r.m = (uint32_t)(((uint64_t)((1ull << l) - d) << 32) / d + 1u);
-    r.s = l - 1u;
-  }
-  return r;
-}
-// The same for divisors up to kMaxUnitPages, with a double-precision division
-// in place of the 64-bit integer one, which on the device is a long routine
-// (the plan kernel's first wave makes every divisor of a plan before anything
-// else can go on): the dividend stays below 2^42, so the quotient's fraction,
-// at least 1 / 1024 away from an integer it does not equal, survives the
-// rounding to 53 bits and the truncation is exact.  With the candidate sizes
-// divided once each the plan kernel takes 7.8 -> 6.9 us for 4 long histories,
-// 13.2 -> 11.9 for 128 listed rows.
-SPLASH_HD UDiv udiv_make_small(uint32_t d) {
   UDiv r;
   r.d = d;
   r.m = 0;

@@ -2,8 +2,9 @@
 
 The planner divides every tile's page count by each candidate unit size; the
 device does this with a multiply-high by a per-divisor magic number
-(`udiv_make` / `udiv` in splash_common.hpp, shared verbatim by host and
-device).  This test compiles that header with the host compiler and compares
+(`udiv` and, for the divisors the planner uses, `udiv_make` in
+splash_common.hpp, shared verbatim by host and device; `udiv_make_int` below
+makes the numbers for any divisor in integers).  This test compiles that header with the host compiler and compares
 the result with plain integer division: exhaustively over every divisor the
 planner can use (1 .. 1024 pages, plus a margin) for all numerators below
 2^17, and over numerators next to multiples of the divisor across the whole
@@ -19,15 +20,27 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2609_37626_amd", "csrc")
 
-PROGRAM = r"""
+REFERENCE = r"""
 #include <stdio.h>
 #include <stdint.h>
 #include "splash_common.hpp"
 using namespace splash;
+static UDiv udiv_make_int(uint32_t d) {
+  UDiv r = {0, 0, d};
+  if (d >= 2) {
+    const uint32_t l = 32u - (uint32_t)__builtin_clz(d - 1u);  // ceil(log2 d)
+    r.m = (uint32_t)(((uint64_t)((1ull << l) - d) << 32) / d + 1u);
+    r.s = l - 1u;
+  }
+  return r;
+}
+"""
+
+PROGRAM = REFERENCE + r"""
 int main() {
   long bad = 0, checked = 0;
   for (uint32_t d = 1; d <= 1100; ++d) {
-    const UDiv u = udiv_make(d);
+    const UDiv u = udiv_make_int(d);
     for (uint32_t n = 0; n < (1u << 17); ++n, ++checked)
       if (udiv(n, u) != n / d) { if (bad++ < 5) printf("d=%u n=%u got %u\n", d, n, udiv(n, u)); }
     // numerators next to multiples of d across the 32-bit range
@@ -44,7 +57,7 @@ int main() {
   }
   // divisors across the whole supported range
   for (uint64_t d = 2; d <= 0x80000000ull; d = d * 5 / 3 + 1) {
-    const UDiv u = udiv_make((uint32_t)d);
+    const UDiv u = udiv_make_int((uint32_t)d);
     for (uint64_t n = 0; n <= 0xffffffffull; n += 0x10001ull * 7 + d) {
       ++checked;
       if (udiv((uint32_t)n, u) != (uint32_t)(n / d)) { if (bad++ < 5) printf("d=%llu n=%llu\n", (unsigned long long)d, (unsigned long long)n); }
@@ -74,13 +87,10 @@ def test_magic_division_and_candidate_parts(tmp_path):
     assert res.returncode == 0, res.stdout
 
 
-SMALL_PROGRAM = r"""
-#include <stdio.h>
-#include "splash_common.hpp"
-using namespace splash;
+SMALL_PROGRAM = REFERENCE + r"""
 int main() {
   for (uint32_t d = 1; d <= (uint32_t)kMaxUnitPages; ++d) {
-    const UDiv a = udiv_make(d), b = udiv_make_small(d);
+    const UDiv a = udiv_make_int(d), b = udiv_make(d);
     if (a.m != b.m || a.s != b.s || a.d != b.d) { printf("d=%u\n", d); return 1; }
   }
   printf("ok\n");
