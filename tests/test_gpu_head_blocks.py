@@ -3,6 +3,9 @@ heads, 4 for at most 64 heads, 2 for at most 32) on both sides of each line,
 for every cache format and at step and page edges, dense and over listed
 positions, against the fp64 oracle with the parity bar of the dense tests
 (bf16 rounding of the output and of the weights)."""
+import dataclasses
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -55,3 +58,24 @@ def test_head_blocks_listed_positions(heads, kv):
                              torch.from_numpy(count).cuda(), out, lse, db.desc(), db.workspace())
     torch.cuda.synchronize()
     check(batch, out, lse, ref)
+
+
+@functools.lru_cache(maxsize=1)
+def many_tiles(kv, q):
+    # more tiles than workers, of differing lengths: a worker runs several units,
+    # longest first (with query chunks a request's side by side)
+    rng = np.random.default_rng(q)
+    lengths = rng.integers(3, 131, 270) if q == 1 else rng.integers(q, 700, 40)
+    batch = W.make_custom(lengths, H=64, q_chunk=q, kv_dtype=kv, seed=q)
+    return batch, oracle.mla_attention(batch.q, batch.kv, batch.block_table, batch.seq_lens, q, batch.softmax_scale,
+                                       kv_dtype=kv, kv_scales=batch.kv_scales)
+
+
+@pytest.mark.parametrize("q,kv,heads", [(q, kv, heads) for q in (1, 8)
+                                        for kv in (W.KV_BF16, W.KV_FP8_E4M3, W.KV_FP8_LATENT) for heads in (32, 64)])
+def test_head_blocks_several_units_a_worker(q, kv, heads):
+    batch, ref = many_tiles(kv, q)
+    assert len(ref[0]) > B.device_workers()
+    few = dataclasses.replace(batch, q=np.ascontiguousarray(batch.q[:, :heads]), H=heads)
+    out, lse = to_device(few).attend()
+    check(few, out, lse, (ref[0][:, :heads], ref[1][:, :heads]))
