@@ -632,8 +632,8 @@ def main():
 
 def measured_peaks(torch, stream):
     """Streaming-read bandwidth (1 GiB, non-temporal 16-byte loads, best of
-    five) and bf16 MFMA rate on random N(0,1) operands (every CU, four
-    chains per wave, best of three), from the calibration library."""
+    five) and bf16 MFMA rate on random N(0,1) operands (every CU, 64 16x16x32
+    tiles per wave, best of three), from the calibration library."""
     import numpy as np
     G = B.device_workers()
     buf = torch.empty(1 << 30, dtype=torch.uint8, device="cuda")
@@ -651,7 +651,7 @@ def measured_peaks(torch, stream):
     ops_bytes = CAL.mfma_ops_bytes(G)
     g = torch.Generator(device="cuda").manual_seed(0)
     ops = torch.randn(ops_bytes // 2, generator=g, device="cuda").to(torch.bfloat16)
-    iters = 1000
+    iters = 10000   # some 5 ms: a short loop ends before the clock settles
     best_mfma = 0.0
     for _ in range(3):
         ev[0].record(stream)
@@ -660,7 +660,7 @@ def measured_peaks(torch, stream):
         torch.cuda.synchronize()
         best_mfma = max(best_mfma, CAL.mfma_flops(G, iters) / (ev[0].elapsed_time(ev[1]) * 1e-3) / 1e12)
     return {"stream_read_gbps": round(best_read, 1), "mfma_random_tflops": round(best_mfma, 1),
-            "how": "streaming read of 1 GiB (2 x CUs workgroups, best of 5); bf16 32x32x16 MFMA loop on "
+            "how": "streaming read of 1 GiB (2 x CUs workgroups, best of 5); bf16 16x16x32 MFMA loop on "
                    "random N(0,1) operands on every CU (best of 3)"}
 
 

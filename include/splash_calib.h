@@ -29,8 +29,8 @@ int splash_calib_stream_read(const void* buf, size_t bytes, void* sink, int32_t 
  * thread. */
 size_t splash_calib_mfma_ops_bytes(int32_t blocks);
 
-/* `iters` rounds of 16 v_mfma_f32_32x32x16_bf16 per wave in four independent
- * accumulation chains, operands from `ops` (splash_calib_mfma_ops_bytes
+/* `iters` rounds of 64 v_mfma_f32_16x16x32_bf16 per wave, one for each of 64
+ * accumulator tiles, operands from `ops` (splash_calib_mfma_ops_bytes
  * bytes, bf16).  `sink`: one float per thread (blocks * 1024 bytes). */
 int splash_calib_mfma_loop(const void* ops, int32_t iters, void* sink, int32_t blocks, void* stream);
 
