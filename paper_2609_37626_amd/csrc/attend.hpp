@@ -41,12 +41,14 @@
 //  * Epilogue: O/l goes through LDS as bf16 (fp16 for a split unit's partial,
 //    with a power-of-two scale per 128 columns) so that every store writes
 //    whole 256-byte row pieces.
-//  * fp8 cache: E4M3 codes convert exactly to bf16; the per-token scale is
-//    applied in fp32 to the score and to P before P is rounded for PV.
+//  * fp8 cache: for QK, K's codes go to the fp8 pipe as they are (exact QK:
+//    they convert exactly to bf16, a fragment ahead of its MFMAs); V's codes
+//    convert exactly to bf16; the per-token scale is applied in fp32 to the
+//    score and to P before P is rounded for PV.
 //  * fp8 latent-row cache (656-byte rows: E4M3 latent with a power-of-two
-//    scale per 128 columns, bf16 RoPE): K tiles convert with their scale;
-//    for PV, wave w's output columns are tile w, so its P weights take the
-//    keys' tile-w scales.
+//    scale per 128 columns, bf16 RoPE): K takes each tile's scale as its block
+//    scale (exact QK: in the conversion); for PV, wave w's output columns are
+//    tile w, so its P weights take the keys' tile-w scales.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -116,9 +118,12 @@ __device__ __forceinline__ float head_sum(float v) {
 // term is off by at most 2^-14.  K enters as the cache's own codes (latent
 // rows: with each tile's power-of-two scale as the A operand's block
 // scale).  S = scale * (K hi^T + 2^-4 K lo^T), two 16x16x128 MFMAs per 128
-// dims and tile, with no per-step conversion of K.  The fp8 MFMA sums its
-// products to about 2^-18 of their magnitude sum (measured), where the bf16
-// MFMA keeps fp32: a score is off by up to about 2^-18 * sum |q_i k_i| * scale.
+// dims and tile, with no per-step conversion of K.  Where the bf16 MFMA keeps
+// fp32 (5e-8 of the magnitude sum at most), the fp8 MFMA aligns the products of
+// a lane's K values to the largest of them and drops what lies below 2^-13 of
+// it (32x32x64 alike).  Over 262,144 sums of 576 products, query N(0, 1) split
+// in two and K N(0, 1) codes, it is off by up to 5.8e-6 of sum |q_i k_i|, 7.5e-7
+// on average (32x32x64: up to 7.0e-6 and 7.5e-7 on the same rows).
 
 // N pairs of bf16 values (one pair per dword of w, low half first) -> hi
 // codes of the values over `unit` (a power of two) and lo codes (the residual
@@ -496,8 +501,9 @@ void attend_kernel(AttendLaunch a) {
   constexpr auto converts = [](int f) { return f < 36 && !(LAT && f % kKS >= 16); };
   // Unit overlap (dense bf16 and per-token fp8): the next unit's query and
   // first kDist steps are issued before this unit's epilogue stores, so their
-  // latency hides behind the epilogue.  (Latent rows: with it the step loop
-  // spills a register, whose reload waits for the loads in flight.)
+  // latency hides behind the epilogue.  (Latent rows: with it the 8-block
+  // kernel's step loop spills a register, whose reload waits for the loads in
+  // flight.)
   constexpr bool kOverlap = !TOPK && !LAT;
   // LDS map: the ring, then the P exchange area (two steps), then (top-k
   // only) the unit's resolved pool rows.  The epilogue's staging (the
