@@ -27,10 +27,13 @@ def unit_size(pages, q_chunk, G, max_partials=1024, unit_cap=1024, listed=False,
             continue
         # two whole tiles of at most `pair` pages, their costs included, take
         # no longer than one unit; a tile stands in the queue where its
-        # request's longest row puts it (lists: anywhere)
+        # request's longest row puts it (lists: anywhere; past 8,192 tiles the
+        # queue is in tile order)
         pair = (16 * c - UNIT - (SPLIT if shard else 0)) / 32
         if q_chunk > 1 and not shard:
             pair = 0 if listed else pair - -(-(q_chunk - 1) // 64)
+        if len(P) > 8192:
+            pair = 0
         free = G < W and 2 * (W - G) <= int(((P >= 1) & (P <= pair)).sum())
         R = 1 if free else -(-W // G)
         cost = max(R * c * 16 * G, 16 * int(P.sum())) + (R * UNIT + min(R, -(-S // G)) * SPLIT) * G + S * COMBINE

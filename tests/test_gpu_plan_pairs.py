@@ -89,3 +89,21 @@ def test_uneven_lists_of_a_request_do_not_pair(q_chunk, batch, counts):
     assert free == (q_chunk == 1)
     if free:
         assert E.busiest(units, G) <= 16 * min(size, 32) + E.UNIT
+
+
+def test_a_queue_in_tile_order_does_not_pair():
+    # past 8,192 tiles the queue is not ordered by length: 40 long lists and 240
+    # short ones among 8,120 empty ones
+    batch, G, max_partials = 8400, B.device_workers(), 1024
+    q, kv, table, lens, d = shared_pages(np.full(batch, 2048, np.int32), 1)
+    count = np.zeros(batch, np.int32)
+    count[::35] = 64
+    count[7:8400:210] = 2048
+    ws = torch.zeros(B.workspace_size(batch, 1, 16, max_partials), dtype=torch.uint8, device="cuda")
+    out = torch.empty((batch, 16, 512), dtype=torch.bfloat16, device="cuda")
+    lse = torch.empty((batch, 16), dtype=torch.float32, device="cuda")
+    idx = torch.arange(2048, dtype=torch.int32, device="cuda").repeat(batch, 1).contiguous()
+    B.splash_mla_attend_topk(q, kv, table, lens, 1, idx, torch.from_numpy(count).cuda(), out, lse, d, ws)
+    size, units = device_plan(ws, batch, 1, 16, max_partials)
+    want, W, free = E.unit_size(-(-count // 64), 1, G, max_partials, 32, listed=True)
+    assert (size, len(units), free) == (want, W, False)
